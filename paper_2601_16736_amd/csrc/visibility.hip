@@ -6,6 +6,9 @@
 // 64 (round, wave) counts and reserves one contiguous range of the index list
 // with a single atomic, so the list holds ascending runs of up to 4096
 // primitives and the one shared counter sees n/4096 atomics.
+#include <cmath>
+#include <cstring>
+
 #include "device_common.h"
 #include "predicate.h"
 
@@ -90,13 +93,58 @@ __global__ __launch_bounds__(kBlock) void visibility_kernel(const float* __restr
     if (idx != nullptr) block_append(vis, first, idx, count);
 }
 
+// The predicate without divisions, for r = 0 (no radius).
+//
+// u = RN(RN(a / p_z) + cx) with a = RN(fx p_x) and p_z > 0 grows with a / p_z,
+// so u >= 0 and u <= width hold exactly for RN(a / p_z) in [lo, hi], two FP32
+// numbers of the camera (view_edges finds them).  RN(x) >= lo differs from
+// x >= lo only where x is within half a unit of lo's last place, i.e. where
+// |a - lo p_z| <= 2^-24 |lo| p_z; outside a margin of 2^-22 times the largest
+// |edge|, the sign of the fused a - lo p_z decides, as its own rounding is
+// 2^-24 of it.  Points within the margin of an edge (about 1e-4 pixel) are
+// left undecided.
+struct KEdges {
+    float xl, xh, yl, yh;    // the interval of RN(a / p_z) in x and in y
+    float margin;            // 2^-22 max |edge|; a NaN leaves every point undecided
+};
+
+enum { kOutside = 0, kInside = 1, kUndecided = 2 };
+
+__device__ __forceinline__ int visible_fast(float x, float y, float z, const KCamera& c, const KEdges& e)
+{
+#pragma clang fp contract(off)
+    const float px = ((c.R[0] * x + c.R[1] * y) + c.R[2] * z) + c.R[3];
+    const float py = ((c.R[4] * x + c.R[5] * y) + c.R[6] * z) + c.R[7];
+    const float pz = ((c.R[8] * x + c.R[9] * y) + c.R[10] * z) + c.R[11];
+    const float ax = c.fx * px, ay = c.fy * py;
+    const float tx = fminf(__builtin_fmaf(-e.xl, pz, ax), __builtin_fmaf(e.xh, pz, -ax));
+    const float ty = fminf(__builtin_fmaf(-e.yl, pz, ay), __builtin_fmaf(e.yh, pz, -ay));
+    const float t = fminf(tx, ty);
+    // a p_z so small that the margin could lose bits, or overflow, decides nothing
+    const float m = e.margin * pz;
+    const float sum = ax + ay;                 // fminf passes a NaN by
+    const bool zin = pz > c.z_near && pz < c.z_far;
+    const bool in = t > m && m > 0x1p-100f && sum == sum;
+    const bool out = t < -m && m > 0x1p-100f;
+    return !zin || out ? kOutside : in ? kInside : kUndecided;
+}
+
+struct KViewEdges {
+    KEdges e[kMaxViews];
+};
+
 // Several views in one pass: bit v of a primitive's word is its predicate in
 // view v; the union (any bit) feeds the mask and the index list.  The means
-// are read once for all views.
+// are read once for all views.  What bounds it is arithmetic, views x
+// primitives predicates, so without a radius the division-free form decides
+// (some 35 instructions instead of 60) and the few points it leaves undecided
+// are read again and take the divisions, outside the unrolled rounds: eight
+// views of 3M primitives went from 40.0 to 29.6 us.
 template <bool RADIUS>
 __global__ __launch_bounds__(kBlock) void visibility_multi_kernel(const float* __restrict__ means, int64_t ms,
                                                                   const float* __restrict__ radius, int64_t n,
-                                                                  KCameras cams, uint8_t* __restrict__ mask,
+                                                                  KCameras cams, KViewEdges edges,
+                                                                  uint8_t* __restrict__ mask,
                                                                   uint32_t* __restrict__ bits,
                                                                   int32_t* __restrict__ idx, int32_t* count)
 {
@@ -115,9 +163,27 @@ __global__ __launch_bounds__(kBlock) void visibility_multi_kernel(const float* _
     for (int s = 0; s < kVisRounds; ++s) b[s] = 0u;
     for (int v = 0; v < cams.n; ++v) {
         const KCamera& c = cams.c[v];
+        if constexpr (RADIUS) {
 #pragma unroll
-        for (int s = 0; s < kVisRounds; ++s)
-            if (visible_pred(x[s], y[s], z[s], RADIUS ? &rho[s] : nullptr, c)) b[s] |= 1u << v;
+            for (int s = 0; s < kVisRounds; ++s)
+                if (visible_pred(x[s], y[s], z[s], &rho[s], c)) b[s] |= 1u << v;
+        } else {
+            uint32_t open = 0;        // rounds left undecided
+#pragma unroll
+            for (int s = 0; s < kVisRounds; ++s) {
+                const int d = visible_fast(x[s], y[s], z[s], c, edges.e[v]);
+                b[s] |= d == kInside ? 1u << v : 0u;
+                open |= d == kUndecided ? 1u << s : 0u;
+            }
+            while (open != 0) {
+                const int r = __builtin_ctz(open);
+                open &= open - 1;
+                const int64_t i = min(first + r * kBlock + threadIdx.x, n - 1);
+                const bool in = visible_pred(means[ms * i], means[ms * i + 1], means[ms * i + 2], nullptr, c);
+#pragma unroll
+                for (int s = 0; s < kVisRounds; ++s) b[s] |= in && s == r ? 1u << v : 0u;
+            }
+        }
     }
     bool vis[kVisRounds];
 #pragma unroll
@@ -150,6 +216,60 @@ __global__ __launch_bounds__(kBlock) void compact_kernel(const uint8_t* __restri
 __global__ void clear_count_kernel(int32_t* count)
 {
     if (threadIdx.x == 0) count[0] = 0;
+}
+
+namespace {
+
+// A finite float's place in their order, and back (both zeros at 0).
+int32_t order_of(float f)
+{
+    int32_t k;
+    memcpy(&k, &f, 4);
+    return k < 0 ? INT32_MIN - k : k;
+}
+
+float float_of(int32_t k)
+{
+    const int32_t b = k < 0 ? INT32_MIN - k : k;
+    float f;
+    memcpy(&f, &b, 4);
+    return f;
+}
+
+// The least finite q with RN(q + centre) >= 0 and the greatest with
+// RN(q + centre) <= size: rounding is monotonic, so each is found by halving.
+void edge_interval(float centre, float size, float* lo, float* hi)
+{
+    const int32_t most = order_of(3.402823466e38f);
+    int32_t a = -most, b = most;
+    while (a < b) {
+        const int32_t m = (int32_t)(((int64_t)a + b) >> 1);
+        volatile float u = float_of(m) + centre;
+        if (u >= 0.0f) b = m;
+        else a = m + 1;
+    }
+    *lo = float_of(a);
+    a = -most;
+    b = most;
+    while (a < b) {
+        const int32_t m = (int32_t)(((int64_t)a + b + 1) >> 1);
+        volatile float u = float_of(m) + centre;
+        if (u <= size) a = m;
+        else b = m - 1;
+    }
+    *hi = float_of(a);
+}
+
+}  // namespace
+
+static KEdges view_edges(const KCamera& c)
+{
+    KEdges e;
+    edge_interval(c.cx, c.W, &e.xl, &e.xh);
+    edge_interval(c.cy, c.H, &e.yl, &e.yh);
+    const float most = fmaxf(fmaxf(fabsf(e.xl), fabsf(e.xh)), fmaxf(fabsf(e.yl), fabsf(e.yh)));
+    e.margin = most < 0x1p60f ? most * 0x1p-22f : NAN;
+    return e;
 }
 
 hipError_t launch_visibility(const float* means, int64_t ms, const float* radius, int64_t n, const KCamera& cam,
@@ -191,13 +311,17 @@ hipError_t launch_visibility_multi(const float* means, int64_t ms, const float* 
         if (e != hipSuccess) return e;
     }
     if (n == 0) return hipSuccess;
+    KViewEdges edges;
+    memset(&edges, 0, sizeof edges);
+    if (radius == nullptr)
+        for (int v = 0; v < cams.n; ++v) edges.e[v] = view_edges(cams.c[v]);
     const unsigned blocks = (unsigned)((n + kVisPerBlock - 1) / kVisPerBlock);
     if (radius != nullptr)
         hipLaunchKernelGGL(visibility_multi_kernel<true>, dim3(blocks), dim3(kBlock), 0, stream, means, ms, radius,
-                           n, cams, mask, bits, idx, count);
+                           n, cams, edges, mask, bits, idx, count);
     else
         hipLaunchKernelGGL(visibility_multi_kernel<false>, dim3(blocks), dim3(kBlock), 0, stream, means, ms, radius,
-                           n, cams, mask, bits, idx, count);
+                           n, cams, edges, mask, bits, idx, count);
     return hipGetLastError();
 }
 
