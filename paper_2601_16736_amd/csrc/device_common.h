@@ -70,7 +70,8 @@ __device__ __forceinline__ int lanes_below(uint64_t mask)
 // Attribute and moment streams are touched once per step.  Their 8- and
 // 16-byte accesses carry the non-temporal hint; 2- and 4-byte ones do not
 // (on the 3M-primitive scene, hinting no access made the step 29 % slower
-// and hinting every access 7 % slower than this split).
+// and hinting every access 7 % slower than this split).  Three elements in one
+// 12- or 6-byte access are hinted or not by rows_in_runs below.
 constexpr bool kNtWide = true;     // 8- and 16-byte loads and stores
 constexpr bool kNtNarrow = false;  // 2- and 4-byte loads and stores
 
@@ -98,11 +99,15 @@ template <typename T, bool NT> __device__ __forceinline__ void st(T* p, T x)
     else *to_global(p) = x;
 }
 
-template <int V> __device__ __forceinline__ void load_f(const float* p, float* x)
+template <int V, bool NT3 = false> __device__ __forceinline__ void load_f(const float* p, float* x)
 {
     if constexpr (V == 4) {
         const f32x4 t = ld<f32x4, kNtWide>(reinterpret_cast<const f32x4*>(p));
         x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
+    } else if constexpr (V == 3) {
+        // joined to one 12-byte access, at any element's alignment
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[q] = ld<float, NT3>(p + q);
     } else if constexpr (V == 2) {
         const f32x2 t = ld<f32x2, kNtWide>(reinterpret_cast<const f32x2*>(p));
         x[0] = t.x; x[1] = t.y;
@@ -111,12 +116,15 @@ template <int V> __device__ __forceinline__ void load_f(const float* p, float* x
     }
 }
 
-template <int V> __device__ __forceinline__ void store_f(float* p, const float* x)
+template <int V, bool NT3 = false> __device__ __forceinline__ void store_f(float* p, const float* x)
 {
     if constexpr (V == 4) {
         f32x4 t;
         t.x = x[0]; t.y = x[1]; t.z = x[2]; t.w = x[3];
         st<f32x4, kNtWide>(reinterpret_cast<f32x4*>(p), t);
+    } else if constexpr (V == 3) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) st<float, NT3>(p + q, x[q]);
     } else if constexpr (V == 2) {
         f32x2 t;
         t.x = x[0]; t.y = x[1];
@@ -132,6 +140,9 @@ template <int V> __device__ __forceinline__ void load_h(const uint16_t* p, float
         const u32x2 t = ld<u32x2, kNtWide>(reinterpret_cast<const u32x2*>(p));
         x[0] = bf16_to_f32(t.x & 0xFFFFu); x[1] = bf16_to_f32(t.x >> 16);
         x[2] = bf16_to_f32(t.y & 0xFFFFu); x[3] = bf16_to_f32(t.y >> 16);
+    } else if constexpr (V == 3) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[q] = bf16_to_f32(ld<uint16_t, kNtNarrow>(p + q));
     } else if constexpr (V == 2) {
         const uint32_t t = ld<uint32_t, kNtNarrow>(reinterpret_cast<const uint32_t*>(p));
         x[0] = bf16_to_f32(t & 0xFFFFu); x[1] = bf16_to_f32(t >> 16);
@@ -146,6 +157,9 @@ template <int V> __device__ __forceinline__ void store_h(uint16_t* p, const uint
         u32x2 t;
         t.x = h[0] | (h[1] << 16); t.y = h[2] | (h[3] << 16);
         st<u32x2, kNtWide>(reinterpret_cast<u32x2*>(p), t);
+    } else if constexpr (V == 3) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) st<uint16_t, kNtNarrow>(p + q, (uint16_t)h[q]);
     } else if constexpr (V == 2) {
         st<uint32_t, kNtNarrow>(reinterpret_cast<uint32_t*>(p), h[0] | (h[1] << 16));
     } else {
@@ -153,10 +167,10 @@ template <int V> __device__ __forceinline__ void store_h(uint16_t* p, const uint
     }
 }
 
-template <bool BF16, int V> __device__ __forceinline__ void load_moment(const void* base, int64_t e, float* x)
+template <bool BF16, int V, bool NT3 = false> __device__ __forceinline__ void load_moment(const void* base, int64_t e, float* x)
 {
     if constexpr (BF16) load_h<V>(static_cast<const uint16_t*>(base) + e, x);
-    else load_f<V>(static_cast<const float*>(base) + e, x);
+    else load_f<V, NT3>(static_cast<const float*>(base) + e, x);
 }
 
 // The 32 rounding bits of element e from draw d = output (e/2 + 1) of
@@ -169,7 +183,7 @@ __device__ __forceinline__ uint32_t sr_word(uint64_t d, int64_t e) { return (e &
 // rounding bits (for V > 1 both are multiples of V: vector access needs
 // dim % V == 0 and a row stride that is a multiple of V).  BF16 with
 // stochastic rounding takes the bits of sr_word.
-template <bool BF16, int V>
+template <bool BF16, int V, bool NT3 = false>
 __device__ __forceinline__ void store_moments(void* mb, void* vb, int64_t e, int64_t el, const float* m,
                                               const float* v, bool sr, uint64_t s2)
 {
@@ -180,6 +194,19 @@ __device__ __forceinline__ void store_moments(void* mb, void* vb, int64_t e, int
                 const uint32_t w = sr_word(d_splitmix(s2, (uint64_t)(el >> 1) + 1), el);
                 hm[0] = f32_to_bf16_sr(m[0], w >> 16);
                 hv[0] = f32_to_bf16_sr(v[0], w & 0xFFFFu);
+            } else if constexpr (V == 3) {
+                // three elements lie in two pairs
+                const uint64_t s = s2 + ((uint64_t)(el >> 1) + 1) * kGamma;
+                const uint64_t d0 = d_mix64(s), d1 = d_mix64(s + kGamma);
+                const bool odd = el & 1;
+                const uint32_t w[3] = {odd ? (uint32_t)d0 : (uint32_t)(d0 >> 32),
+                                       odd ? (uint32_t)(d1 >> 32) : (uint32_t)d0,
+                                       odd ? (uint32_t)d1 : (uint32_t)(d1 >> 32)};
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    hm[q] = f32_to_bf16_sr(m[q], w[q] >> 16);
+                    hv[q] = f32_to_bf16_sr(v[q], w[q] & 0xFFFFu);
+                }
             } else {
 #pragma unroll
                 for (int q = 0; q < V; q += 2) {
@@ -201,8 +228,8 @@ __device__ __forceinline__ void store_moments(void* mb, void* vb, int64_t e, int
         store_h<V>(static_cast<uint16_t*>(mb) + e, hm);
         store_h<V>(static_cast<uint16_t*>(vb) + e, hv);
     } else {
-        store_f<V>(static_cast<float*>(mb) + e, m);
-        store_f<V>(static_cast<float*>(vb) + e, v);
+        store_f<V, NT3>(static_cast<float*>(mb) + e, m);
+        store_f<V, NT3>(static_cast<float*>(vb) + e, v);
     }
 }
 
@@ -299,14 +326,14 @@ __device__ __forceinline__ void update_element(float& th, float g, float& m, flo
 // One group's read-modify-write pass over the wave's staged rows.  Each
 // lane takes U (row, chunk) items per trip and issues all their loads before
 // any store, so a wave keeps U x 4 vector loads in flight.  NOISE (mean
-// group only, V = 1) subtracts the position-noise displacement, staged per
-// row in s_noise, after the Adam update.
-template <bool BF16, int V, int U, bool NOISE = false>
+// group only, V = 1 or 3) subtracts the position-noise displacement, staged per
+// row in s_noise, after the Adam update.  NT3: the non-temporal hint for V = 3.
+template <bool BF16, int V, int U, bool NOISE = false, bool NT3 = false>
 __device__ __forceinline__ void step_group(const KGroup& G, const KHyper& H, int nrows,
                                            const int* s_row, const float* s_rb1, const float* s_rsb2,
                                            int lane, float dar_scale, uint64_t sr_s2, const float* s_noise = nullptr)
 {
-    const int cpr = G.cpr;
+    const int cpr = V == 1 ? G.dim : G.cpr;
     const int dim = G.dim;
     const int64_t stride = G.stride;
     const int items = nrows * cpr;
@@ -323,7 +350,7 @@ __device__ __forceinline__ void step_group(const KGroup& G, const KHyper& H, int
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             ok[u] = k0 + u * kWave < items;
-            nidx[u] = 3 * r + c;
+            nidx[u] = 3 * r + c * V;
             const int raw = ok[u] ? s_row[r] : 0;
             // a row in this iteration's Re-State sample decays by alpha before
             // the moment update: beta*(alpha*m) folded into (beta*alpha)*m
@@ -341,10 +368,10 @@ __device__ __forceinline__ void step_group(const KGroup& G, const KHyper& H, int
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (ok[u]) {
-                load_f<V>(G.param + e[u], th[u]);
-                load_f<V>(G.grad + e[u], g[u]);
-                load_moment<BF16, V>(G.m, e[u], m[u]);
-                load_moment<BF16, V>(G.v, e[u], v[u]);
+                load_f<V, NT3>(G.param + e[u], th[u]);
+                load_f<V, NT3>(G.grad + e[u], g[u]);
+                load_moment<BF16, V, NT3>(G.m, e[u], m[u]);
+                load_moment<BF16, V, NT3>(G.v, e[u], v[u]);
             }
         }
 #pragma unroll
@@ -354,10 +381,10 @@ __device__ __forceinline__ void step_group(const KGroup& G, const KHyper& H, int
             for (int q = 0; q < V; ++q) {
                 update_element(th[u][q], g[u][q], m[u][q], v[u][q], c1[u], c2[u], rb1[u], rsb2[u], H, dar,
                                G.dar_kind, G.reg_mode, dar_scale, G.dar_clip, G.lr);
-                if constexpr (NOISE) th[u][q] -= s_noise[nidx[u]];     // the mean group: dim 3, V = 1
+                if constexpr (NOISE) th[u][q] -= s_noise[nidx[u] + q];     // the mean group: dim 3
             }
-            store_f<V>(G.param + e[u], th[u]);
-            store_moments<BF16, V>(G.m, G.v, e[u], el[u], m[u], v[u], H.sr != 0, sr_s2);
+            store_f<V, NT3>(G.param + e[u], th[u]);
+            store_moments<BF16, V, NT3>(G.m, G.v, e[u], el[u], m[u], v[u], H.sr != 0, sr_s2);
         }
     }
 }
@@ -676,6 +703,35 @@ __device__ __forceinline__ void step_packed(const KScene& S, const KHyper& H, ui
     }
 }
 
+// Rows that are no multiple of 16 bytes move three elements at a time if they
+// can (dim 3, 9, 15, 45 ..).  A wave writes a run of such rows whole but for its
+// ends, and the non-temporal hint then pays as it does for wider accesses;
+// isolated rows end inside 64-byte segments, which hinted stores write to memory
+// in parts.  Whole step, groups 3+3+4+1+3+45, us, one element at a time / three
+// / three and hinted: 3M Morton view 351 / 351 / 302; 600k rows, all visible,
+// 203 / 201 / 179; 1.2M unsorted, 30 % visible, 284 / 284 / 304.
+// Groups of one access per row stay in the 256 MB Infinity Cache from step to
+// step up to about 2M rows unless hinted past it (two groups of 3 FP32: 96 bytes
+// a row): 600k rows all visible 175 without the hint, 186 with it; 3M Morton
+// view, 3+3+4+1+48, 298 and 283, in BF16 221 and 214.
+// Isolated 3-element rows of BF16 moments are better read element by element
+// (five unsorted scenes, 3M rows in all: 447 us, three at a time 459).
+constexpr int64_t kNtRows = (int64_t)1 << 21;
+
+// Whether the staged rows lie in runs of four rows or more on average.  The line
+// is not a sharp one (eight gives the same times to 2 %): random rows make runs
+// of 1.4 at 30 % and 2.5 at 60 % visible, ordered scenes runs of whole windows.
+__device__ __forceinline__ bool rows_in_runs(int nrows, const int* s_row, int lane)
+{
+    int breaks = 0;
+    for (int j0 = 0; j0 < nrows; j0 += kWave) {
+        const int j = j0 + lane;
+        const bool starts = j < nrows && (j == 0 || (s_row[j] & 0x7FFFFFFF) != (s_row[j - 1] & 0x7FFFFFFF) + 1);
+        breaks += __popcll(__ballot(starts));
+    }
+    return breaks * 4 <= nrows;
+}
+
 // Every group's pass over the staged rows.  U: (row, chunk) items per lane
 // per trip for the 16/8-byte groups (twice that for 4-byte ones, the noise
 // group included).
@@ -712,7 +768,7 @@ __device__ __forceinline__ void step_all_groups(const KScene& S, const KHyper& H
             noise_row(nz, (int64_t)(s_row[j] & 0x7FFFFFFF), H.noise_k, H.noise_t, &s_noise[3 * j]);
         wave_sync();
         if (!PACKED || S.pk_stride == 0)
-            step_group<BF16, 1, U * 2, true>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2, s_noise);
+            step_group<BF16, 3, U, true>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2, s_noise);
     }
     // the packed pass is compiled only into the kernels for packed scenes, so
     // the per-group kernels keep their register budget
@@ -722,6 +778,7 @@ __device__ __forceinline__ void step_all_groups(const KScene& S, const KHyper& H
             return;
         }
     }
+    const bool runs = rows_in_runs(nrows, s_row, lane);
     for (int gi = 0; gi < S.n_groups; ++gi) {
         if (gi == first) continue;
         const KGroup& G = S.g[gi];
@@ -731,6 +788,8 @@ __device__ __forceinline__ void step_all_groups(const KScene& S, const KHyper& H
                                     : (float)G.dar_lambda;
         const uint64_t s2 = BF16 ? d_stream(seed, kTagSrStep + (uint64_t)gi, H.iteration) : 0;
         if (G.vec == 4) step_group<BF16, 4, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
+        else if (G.vec == 3 && runs && (G.cpr > 1 || S.n >= kNtRows)) step_group<BF16, 3, U, false, true>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
+        else if (G.vec == 3 && (!BF16 || runs || G.cpr > 1)) step_group<BF16, 3, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
         else if (G.vec == 2) step_group<BF16, 2, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
         else step_group<BF16, 1, U * 2>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
     }
@@ -746,6 +805,7 @@ __device__ __forceinline__ void invisible_all_groups(const KScene& S, const KHyp
         const uint64_t s2 = BF16 ? d_stream(seed, kTagSrRsr + (uint64_t)gi, H.iteration) : 0;
         const float lr_aiu = (float)((double)G.lr * H.aiu_scale);
         if (G.vec == 4) invisible_group<BF16, 4>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
+        else if (G.vec == 3) invisible_group<BF16, 3>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
         else if (G.vec == 2) invisible_group<BF16, 2>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
         else invisible_group<BF16, 1>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
     }

@@ -24,7 +24,7 @@ struct KGroup {
     void* m;
     void* v;
     int32_t dim;
-    int32_t vec;         // elements per access: 4, 2 or 1
+    int32_t vec;         // elements per access: 4, 3, 2 or 1
     int32_t cpr;         // accesses per row = dim / vec
     float lr;
     int32_t dar_kind;

@@ -465,6 +465,7 @@ __global__ __launch_bounds__(kBlock) void select_write_kernel(const float* __res
     for (int gi = 0; gi < S.n_groups; ++gi) {
         const KGroup& G = S.g[gi];
         if (G.vec == 4) zero_group<BF16, 4>(G, nrows, s_row[wave], lane);
+        else if (G.vec == 3) zero_group<BF16, 3>(G, nrows, s_row[wave], lane);
         else if (G.vec == 2) zero_group<BF16, 2>(G, nrows, s_row[wave], lane);
         else zero_group<BF16, 1>(G, nrows, s_row[wave], lane);
     }
