@@ -710,14 +710,11 @@ __device__ __forceinline__ void step_packed(const KScene& S, const KHyper& H, ui
 // in parts.  Whole step, groups 3+3+4+1+3+45, us, one element at a time / three
 // / three and hinted: 3M Morton view 351 / 351 / 302; 600k rows, all visible,
 // 203 / 201 / 179; 1.2M unsorted, 30 % visible, 284 / 284 / 304.
-// Groups of one access per row stay in the 256 MB Infinity Cache from step to
-// step up to about 2M rows unless hinted past it (two groups of 3 FP32: 96 bytes
-// a row): 600k rows all visible 175 without the hint, 186 with it; 3M Morton
-// view, 3+3+4+1+48, 298 and 283, in BF16 221 and 214.
+// Groups of one access per row are never hinted: they stay in the 256 MB Infinity
+// Cache from step to step (600k rows all visible 175 without the hint, 186 with
+// it; 3M Morton views that follow one another 269 and 281).
 // Isolated 3-element rows of BF16 moments are better read element by element
 // (five unsorted scenes, 3M rows in all: 447 us, three at a time 459).
-constexpr int64_t kNtRows = (int64_t)1 << 21;
-
 // Whether the staged rows lie in runs of four rows or more on average.  The line
 // is not a sharp one (eight gives the same times to 2 %): random rows make runs
 // of 1.4 at 30 % and 2.5 at 60 % visible, ordered scenes runs of whole windows.
@@ -788,7 +785,7 @@ __device__ __forceinline__ void step_all_groups(const KScene& S, const KHyper& H
                                     : (float)G.dar_lambda;
         const uint64_t s2 = BF16 ? d_stream(seed, kTagSrStep + (uint64_t)gi, H.iteration) : 0;
         if (G.vec == 4) step_group<BF16, 4, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
-        else if (G.vec == 3 && runs && (G.cpr > 1 || S.n >= kNtRows)) step_group<BF16, 3, U, false, true>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
+        else if (G.vec == 3 && runs && G.cpr > 1) step_group<BF16, 3, U, false, true>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
         else if (G.vec == 3 && (!BF16 || runs || G.cpr > 1)) step_group<BF16, 3, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
         else if (G.vec == 2) step_group<BF16, 2, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
         else step_group<BF16, 1, U * 2>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
