@@ -178,19 +178,16 @@ gs_status build_groups(const gs_group* groups, int32_t n_groups, int64_t n, int3
         K.m = G.exp_avg;
         K.v = G.exp_avg_sq;
         K.dim = G.dim;
-        // a row's accesses are as wide as its length, stride and pointers allow;
-        // three elements go at any alignment, 12 or 6 bytes in one access or two
-        int vec = 1;
-        if (G.dim % 4 == 0 && stride % 4 == 0 && aligned(G.param, 16) && aligned(G.grad, 16) &&
-            aligned(G.exp_avg, 4 * msz) && aligned(G.exp_avg_sq, 4 * msz))
-            vec = 4;
-        else if (G.dim % 2 == 0 && stride % 2 == 0 && aligned(G.param, 8) && aligned(G.grad, 8) &&
-                 aligned(G.exp_avg, 2 * msz) && aligned(G.exp_avg_sq, 2 * msz))
-            vec = 2;
-        else if (G.dim % 3 == 0)
-            vec = 3;
-        K.vec = vec;
-        K.cpr = G.dim / vec;
+        // what the row's stride and pointers allow
+        const int widest = stride % 4 == 0 && aligned(G.param, 16) && aligned(G.grad, 16) &&
+                                   aligned(G.exp_avg, 4 * msz) && aligned(G.exp_avg_sq, 4 * msz)
+                               ? 4
+                           : stride % 2 == 0 && aligned(G.param, 8) && aligned(G.grad, 8) &&
+                                   aligned(G.exp_avg, 2 * msz) && aligned(G.exp_avg_sq, 2 * msz)
+                               ? 2
+                               : 1;
+        K.vec = access_elements(G.dim, widest, bf16);
+        K.cpr = G.dim / K.vec;
         K.lr = (float)G.lr;
         K.dar_kind = G.dar_kind;
         K.reg_mode = G.reg_mode;

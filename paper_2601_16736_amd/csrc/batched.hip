@@ -53,7 +53,7 @@ struct KBatch {
     int32_t inv_first[kMaxScenes + 1];        // first invisible unit of each scene, after all step units
 };
 
-template <bool BF16, bool NOISE, bool PACKED>
+template <bool BF16, bool NOISE, bool PACKED, bool THREES>
 __device__ __forceinline__ void step_unit(const KScene& S, const KHyper& H, int64_t local, int* s_row, float* s_rb1,
                                           float* s_rsb2, float* s_noise, int lane)
 {
@@ -84,12 +84,12 @@ __device__ __forceinline__ void step_unit(const KScene& S, const KHyper& H, int6
         wave_sync();
         stage_step_rows(nrows, s_row, s_rb1, s_rsb2, S.t, H, d_stream(seed, kTagRsr, H.iteration), lane);
         wave_sync();
-        step_all_groups<BF16, NOISE, kBatchUnroll, PACKED>(S, H, seed, nrows, s_row, s_rb1, s_rsb2, lane, s_noise);
+        step_all_groups<BF16, NOISE, kBatchUnroll, PACKED, THREES>(S, H, seed, nrows, s_row, s_rb1, s_rsb2, lane, s_noise);
     }
     wave_sync();   // the next unit reuses this wave's LDS rows
 }
 
-template <bool BF16>
+template <bool BF16, bool THREES>
 __device__ __forceinline__ void invisible_unit(const KScene& S, const KHyper& H, int64_t local, int* s_row,
                                                float* s_rb1, float* s_rsb2, int lane)
 {
@@ -100,7 +100,7 @@ __device__ __forceinline__ void invisible_unit(const KScene& S, const KHyper& H,
                                                        lane);
     if (nrows > 0) {
         wave_sync();
-        invisible_all_groups<BF16>(S, H, seed, nrows, s_row, s_rb1, s_rsb2, lane);
+        invisible_all_groups<BF16, THREES>(S, H, seed, nrows, s_row, s_rb1, s_rsb2, lane);
     }
     wave_sync();
 }
@@ -113,7 +113,10 @@ __device__ __forceinline__ int scene_of(const int32_t* first, int n_scenes, int6
     return s;
 }
 
-template <bool BF16, bool NOISE, bool PACKED>
+// THREES: some group of the plan goes three elements at a time (KGroup::vec).
+// A plan without one takes the kernel that leaves those passes out (three scenes
+// of 485,000 rows in all, us: BF16 77.0 without, 78.2 with them).
+template <bool BF16, bool NOISE, bool PACKED, bool THREES>
 __global__ __launch_bounds__(kBlock, PACKED ? 4 : 1) void batched_kernel(KBatch B, KHyper H)
 {
     __shared__ int s_row[kWavesPerBlock][kBatchCap];
@@ -134,13 +137,13 @@ __global__ __launch_bounds__(kBlock, PACKED ? 4 : 1) void batched_kernel(KBatch 
     for (int64_t u = (int64_t)blockIdx.x * kWavesPerBlock + wave; u < total; u += stride) {
         if (u < steps) {
             const int s = scene_of(B.step_first, B.n_scenes, u);
-            step_unit<BF16, NOISE, PACKED>(*(const KScene*)(scenes + s), H, u - B.step_first[s], s_row[wave],
-                                           s_rb1[wave], s_rsb2[wave], s_noise[wave], lane);
+            step_unit<BF16, NOISE, PACKED, THREES>(*(const KScene*)(scenes + s), H, u - B.step_first[s], s_row[wave],
+                                                   s_rb1[wave], s_rsb2[wave], s_noise[wave], lane);
         } else {
             const int64_t v = u - steps;
             const int s = scene_of(B.inv_first, B.n_scenes, v);
-            invisible_unit<BF16>(*(const KScene*)(scenes + s), H, v - B.inv_first[s], s_row[wave], s_rb1[wave],
-                                 s_rsb2[wave], lane);
+            invisible_unit<BF16, THREES>(*(const KScene*)(scenes + s), H, v - B.inv_first[s], s_row[wave],
+                                         s_rb1[wave], s_rsb2[wave], lane);
         }
     }
 }
@@ -156,6 +159,7 @@ struct gs_batch {
     int32_t moment_dtype = 0;
     bool any_adaptive = false;
     bool any_packed = false;                    // some scene has packed rows
+    bool any_threes = false;                    // some group goes three elements at a time
     std::vector<KScene> h_scenes;
     std::vector<int32_t> sched;
     KScene* d_scenes = nullptr;
@@ -170,22 +174,24 @@ struct gs_batch {
 
 namespace {
 
-// packed: some scene of the plan has packed rows (those kernels also carry
-// the per-group passes, for the plan's other scenes)
-void* kernel_for(int moment_dtype, int noise, bool packed)
+template <bool BF16, bool THREES>
+void* kernel_for(int noise, bool packed)
 {
-    if (packed) {
-        if (moment_dtype == GS_MOMENT_BF16)
-            return noise ? reinterpret_cast<void*>(&batched_kernel<true, true, true>)
-                         : reinterpret_cast<void*>(&batched_kernel<true, false, true>);
-        return noise ? reinterpret_cast<void*>(&batched_kernel<false, true, true>)
-                     : reinterpret_cast<void*>(&batched_kernel<false, false, true>);
-    }
-    if (moment_dtype == GS_MOMENT_BF16)
-        return noise ? reinterpret_cast<void*>(&batched_kernel<true, true, false>)
-                     : reinterpret_cast<void*>(&batched_kernel<true, false, false>);
-    return noise ? reinterpret_cast<void*>(&batched_kernel<false, true, false>)
-                 : reinterpret_cast<void*>(&batched_kernel<false, false, false>);
+    if (packed)
+        return noise ? reinterpret_cast<void*>(&batched_kernel<BF16, true, true, THREES>)
+                     : reinterpret_cast<void*>(&batched_kernel<BF16, false, true, THREES>);
+    return noise ? reinterpret_cast<void*>(&batched_kernel<BF16, true, false, THREES>)
+                 : reinterpret_cast<void*>(&batched_kernel<BF16, false, false, THREES>);
+}
+
+// The packed kernels also carry the per-group passes, for the plan's other scenes.
+void* kernel_for(const gs_batch* b, int noise)
+{
+    if (b->moment_dtype == GS_MOMENT_BF16)
+        return b->any_threes ? kernel_for<true, true>(noise, b->any_packed)
+                             : kernel_for<true, false>(noise, b->any_packed);
+    return b->any_threes ? kernel_for<false, true>(noise, b->any_packed)
+                         : kernel_for<false, false>(noise, b->any_packed);
 }
 
 void free_batch(gs_batch* b)
@@ -244,6 +250,14 @@ extern "C" gs_status gs_batch_create(const gs_scene* scenes, int32_t n_scenes, i
         int32_t dims[GS_MAX_GROUPS];
         for (int g = 0; g < sc.n_groups; ++g) {
             dims[g] = sc.groups[g].dim;
+            // rows of three elements go one by one here (five unsorted FP32
+            // scenes, 3M rows of 3+3+4+1+3+45 values in all: 455.6 us, whole
+            // rows 458.9; 485,000 rows of 3+3+4+1+48 values 71.2 and 72.7)
+            if (K.g[g].vec == 3 && K.g[g].cpr == 1) {
+                K.g[g].vec = 1;
+                K.g[g].cpr = K.g[g].dim;
+            }
+            if (K.g[g].vec == 3) b->any_threes = true;
             if (sc.groups[g].dar_kind != GS_DAR_NONE && sc.groups[g].reg_mode == GS_REG_ADAPTIVE) b->any_adaptive = true;
         }
         int sched = 0, unit = 0;
@@ -343,7 +357,7 @@ extern "C" gs_status adamw_gs_step_batched(gs_batch* b, const gs_step_config* cf
     void* args[] = {&b->kb, &b->kh};
     hipKernelNodeParams p;
     memset(&p, 0, sizeof p);
-    p.func = kernel_for(b->moment_dtype, v, b->any_packed);
+    p.func = kernel_for(b, v);
     const int64_t blocks = (units + kWavesPerBlock - 1) / kWavesPerBlock;
     // the waves stride over the units, so a grid capped at one dispatch's
     // limit still covers them all
@@ -383,7 +397,7 @@ extern "C" gs_status gs_batch_set_resident(gs_batch* b, int32_t resident)
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void*>(kernel_for(b->moment_dtype, 0, b->any_packed)), kBlock, 0) != hipSuccess)
+            &per_cu, reinterpret_cast<const void*>(kernel_for(b, 0)), kBlock, 0) != hipSuccess)
         return set_error(GS_EHIP, "gs_batch_set_resident: device query failed");
     b->persistent_blocks = (int64_t)cus * std::max(1, per_cu);
     return GS_OK;

@@ -180,9 +180,10 @@ __device__ __forceinline__ uint32_t sr_word(uint64_t d, int64_t e) { return (e &
 
 // Stores m and v of V consecutive elements at array offset e; el is the
 // first one's element index row * dim + column in its group, which keys its
-// rounding bits (for V > 1 both are multiples of V: vector access needs
-// dim % V == 0 and a row stride that is a multiple of V).  BF16 with
-// stochastic rounding takes the bits of sr_word.
+// rounding bits (for V = 2 and 4 both are multiples of V: such access needs
+// dim % V == 0 and a row stride that is a multiple of V; V = 3 needs only
+// dim % 3 == 0, so both may be odd).  BF16 with stochastic rounding takes the
+// bits of sr_word.
 template <bool BF16, int V, bool NT3 = false>
 __device__ __forceinline__ void store_moments(void* mb, void* vb, int64_t e, int64_t el, const float* m,
                                               const float* v, bool sr, uint64_t s2)
@@ -323,17 +324,30 @@ __device__ __forceinline__ void update_element(float& th, float g, float& m, flo
     v = vv;
 }
 
+// The lane as a value tied to this group (its accesses per row), so that what a
+// BF16 pass computes from it is not kept in registers through the passes of the
+// other groups: the BF16 view step over windows of 32 and 64 holds 80 VGPRs with
+// it, 81 without, i.e. six waves per SIMD against five (3M Morton view 222.1 us
+// against 225.4, 0.7M unsorted rows in four views 106.7 against 110.4).  FP32
+// passes stay below their 128 without it and lose 0.5 % with it.
+template <bool BF16> __device__ __forceinline__ int own_lane(int lane, int cpr)
+{
+    if constexpr (BF16) asm("" : "+v"(lane) : "s"(cpr));
+    return lane;
+}
+
 // One group's read-modify-write pass over the wave's staged rows.  Each
 // lane takes U (row, chunk) items per trip and issues all their loads before
 // any store, so a wave keeps U x 4 vector loads in flight.  NOISE (mean
-// group only, V = 1 or 3) subtracts the position-noise displacement, staged per
+// group only, V = 3) subtracts the position-noise displacement, staged per
 // row in s_noise, after the Adam update.  NT3: the non-temporal hint for V = 3.
 template <bool BF16, int V, int U, bool NOISE = false, bool NT3 = false>
 __device__ __forceinline__ void step_group(const KGroup& G, const KHyper& H, int nrows,
                                            const int* s_row, const float* s_rb1, const float* s_rsb2,
                                            int lane, float dar_scale, uint64_t sr_s2, const float* s_noise = nullptr)
 {
-    const int cpr = V == 1 ? G.dim : G.cpr;
+    const int cpr = NOISE ? 1 : G.cpr;      // the mean group: dim 3, whole rows
+    lane = own_lane<BF16>(lane, cpr);
     const int dim = G.dim;
     const int64_t stride = G.stride;
     const int items = nrows * cpr;
@@ -704,22 +718,26 @@ __device__ __forceinline__ void step_packed(const KScene& S, const KHyper& H, ui
 }
 
 // Rows that are no multiple of 16 bytes move three elements at a time if they
-// can (dim 3, 9, 15, 45 ..).  A wave writes a run of such rows whole but for its
-// ends, and the non-temporal hint then pays as it does for wider accesses;
-// isolated rows end inside 64-byte segments, which hinted stores write to memory
-// in parts.  Whole step, groups 3+3+4+1+3+45, us, one element at a time / three
-// / three and hinted: 3M Morton view 351 / 351 / 302; 600k rows, all visible,
-// 203 / 201 / 179; 1.2M unsorted, 30 % visible, 284 / 284 / 304.
+// can (dim 9, 15, 45 .., FP32 also 3).  A wave writes a run of such rows whole
+// but for its ends, and the non-temporal hint then pays as it does for wider
+// accesses; isolated rows end inside 64-byte segments, which hinted stores write
+// to memory in parts.  Whole step, groups 3+3+4+1+3+45, us, one element at a time
+// / three / three and hinted: 3M Morton view 351 / 351 / 302; 600k rows, all
+// visible, 203 / 201 / 179; 1.2M unsorted, 30 % visible, 284 / 284 / 304; BF16
+// moments, 3M Morton view 288 / 264 / 252, 1M unsorted view 179 / 174 / 186.
 // Groups of one access per row are never hinted: they stay in the 256 MB Infinity
 // Cache from step to step (600k rows all visible 175 without the hint, 186 with
 // it; 3M Morton views that follow one another 269 and 281).
-// Isolated 3-element rows of BF16 moments are better read element by element
-// (five unsorted scenes, 3M rows in all: 447 us, three at a time 459).
-// Whether the staged rows lie in runs of four rows or more on average.  The line
-// is not a sharp one (eight gives the same times to 2 %): random rows make runs
-// of 1.4 at 30 % and 2.5 at 60 % visible, ordered scenes runs of whole windows.
-__device__ __forceinline__ bool rows_in_runs(int nrows, const int* s_row, int lane)
+
+// Whether the staged rows lie in runs of four rows or more on average: the side
+// of the hint's rule.  The line is not a sharp one (eight gives the same times to
+// 2 %): random rows make runs of 1.4 at 30 % and 2.5 at 60 % visible, ordered
+// scenes runs of whole windows.  Asked only where a group has such rows: small
+// views without one lost 0.7 % to it (160,000 FP32 rows 42.3 us, 42.0 now).
+template <bool BF16>
+__device__ __forceinline__ bool rows_in_runs(int nrows, const int* s_row, int lane, int cpr)
 {
+    lane = own_lane<BF16>(lane, cpr);
     int breaks = 0;
     for (int j0 = 0; j0 < nrows; j0 += kWave) {
         const int j = j0 + lane;
@@ -730,9 +748,9 @@ __device__ __forceinline__ bool rows_in_runs(int nrows, const int* s_row, int la
 }
 
 // Every group's pass over the staged rows.  U: (row, chunk) items per lane
-// per trip for the 16/8-byte groups (twice that for 4-byte ones, the noise
-// group included).
-template <bool BF16, bool NOISE, int U, bool PACKED>
+// per trip (twice that for groups that go element by element).  THREES: some
+// group may go three elements at a time.
+template <bool BF16, bool NOISE, int U, bool PACKED, bool THREES = true>
 __device__ __forceinline__ void step_all_groups(const KScene& S, const KHyper& H, uint64_t seed, int nrows,
                                                 const int* s_row, const float* s_rb1, const float* s_rsb2,
                                                 int lane, float* s_noise = nullptr)
@@ -775,7 +793,6 @@ __device__ __forceinline__ void step_all_groups(const KScene& S, const KHyper& H
             return;
         }
     }
-    const bool runs = rows_in_runs(nrows, s_row, lane);
     for (int gi = 0; gi < S.n_groups; ++gi) {
         if (gi == first) continue;
         const KGroup& G = S.g[gi];
@@ -785,14 +802,14 @@ __device__ __forceinline__ void step_all_groups(const KScene& S, const KHyper& H
                                     : (float)G.dar_lambda;
         const uint64_t s2 = BF16 ? d_stream(seed, kTagSrStep + (uint64_t)gi, H.iteration) : 0;
         if (G.vec == 4) step_group<BF16, 4, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
-        else if (G.vec == 3 && runs && G.cpr > 1) step_group<BF16, 3, U, false, true>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
-        else if (G.vec == 3 && (!BF16 || runs || G.cpr > 1)) step_group<BF16, 3, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
         else if (G.vec == 2) step_group<BF16, 2, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
-        else step_group<BF16, 1, U * 2>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
+        else if (!THREES || G.vec == 1) step_group<BF16, 1, U * 2>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
+        else if (G.cpr > 1 && rows_in_runs<BF16>(nrows, s_row, lane, G.cpr)) step_group<BF16, 3, U, false, true>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
+        else step_group<BF16, 3, U>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, dar_scale, s2);
     }
 }
 
-template <bool BF16>
+template <bool BF16, bool THREES = true>
 __device__ __forceinline__ void invisible_all_groups(const KScene& S, const KHyper& H, uint64_t seed, int nrows,
                                                      const int* s_row, const float* s_rb1, const float* s_rsb2,
                                                      int lane)
@@ -802,7 +819,7 @@ __device__ __forceinline__ void invisible_all_groups(const KScene& S, const KHyp
         const uint64_t s2 = BF16 ? d_stream(seed, kTagSrRsr + (uint64_t)gi, H.iteration) : 0;
         const float lr_aiu = (float)((double)G.lr * H.aiu_scale);
         if (G.vec == 4) invisible_group<BF16, 4>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
-        else if (G.vec == 3) invisible_group<BF16, 3>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
+        else if (THREES && G.vec == 3) invisible_group<BF16, 3>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
         else if (G.vec == 2) invisible_group<BF16, 2>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
         else invisible_group<BF16, 1>(G, H, nrows, s_row, s_rb1, s_rsb2, lane, s2, lr_aiu);
     }

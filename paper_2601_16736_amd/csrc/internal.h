@@ -34,6 +34,19 @@ struct KGroup {
     double dar_lambda;   // lambda; the kernels form lambda / N_I' in double, as the host would
 };
 
+// KGroup::vec of rows of dim elements whose stride and pointers allow accesses
+// of `widest` elements (4, 2 or 1).  Three go at any alignment, 12 bytes in one
+// access (6 in two).  Rows of three elements stay one by one with BF16 moments:
+// three at a time made no call faster (3M Morton view 221.9 us both ways at equal
+// waves) and isolated rows slower (five unsorted scenes 447 us, 459).  FP32 ones
+// gain in the two-launch step (100,000 unsorted rows 37.8 us, 36.1).
+inline int access_elements(int dim, int widest, bool bf16)
+{
+    if (widest >= 4 && dim % 4 == 0) return 4;
+    if (widest >= 2 && dim % 2 == 0) return 2;
+    return dim % 3 == 0 && !(bf16 && dim == 3) ? 3 : 1;
+}
+
 // Per-call scalars.
 struct KHyper {
     float beta1, omb1, beta2, omb2;   // beta and (1 - beta), both rounded from double

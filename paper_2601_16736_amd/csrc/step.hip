@@ -11,7 +11,8 @@ namespace gs {
 // The grid covers the largest possible unit count; waves past the end exit.
 // NOISE adds the position-noise displacement to the mean group.
 // Items in flight per lane: four with FP32 moments (faster than two on the
-// 3M scene; 126 VGPRs, no scratch), two with BF16 moments (four spills there).
+// 3M scene; 120 to 124 VGPRs, no scratch), two with BF16 moments (77 and 78,
+// six waves per SIMD; four spills there).
 #ifndef GS_STEP_UNROLL
 #define GS_STEP_UNROLL 4
 #endif

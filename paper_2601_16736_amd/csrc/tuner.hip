@@ -130,7 +130,7 @@ gs_status tune(const char* who, int64_t n, const int32_t* dims, int32_t n_groups
         K.m = bufs[(size_t)g * 4 + 2].p;
         K.v = bufs[(size_t)g * 4 + 3].p;
         K.dim = dims[g];
-        K.vec = dims[g] % 4 == 0 ? 4 : (dims[g] % 2 == 0 ? 2 : (dims[g] % 3 == 0 ? 3 : 1));
+        K.vec = access_elements(dims[g], dims[g] % 4 == 0 ? 4 : dims[g] % 2 == 0 ? 2 : 1, bf16);
         K.cpr = dims[g] / K.vec;
         K.stride = dims[g];
         K.lr = 1e-3f;
