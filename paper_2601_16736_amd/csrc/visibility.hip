@@ -10,6 +10,7 @@
 #include <cstring>
 
 #include "device_common.h"
+#include "edges.h"
 #include "predicate.h"
 
 namespace gs {
@@ -218,57 +219,13 @@ __global__ void clear_count_kernel(int32_t* count)
     if (threadIdx.x == 0) count[0] = 0;
 }
 
-namespace {
-
-// A finite float's place in their order, and back (both zeros at 0).
-int32_t order_of(float f)
-{
-    int32_t k;
-    memcpy(&k, &f, 4);
-    return k < 0 ? INT32_MIN - k : k;
-}
-
-float float_of(int32_t k)
-{
-    const int32_t b = k < 0 ? INT32_MIN - k : k;
-    float f;
-    memcpy(&f, &b, 4);
-    return f;
-}
-
-// The least finite q with RN(q + centre) >= 0 and the greatest with
-// RN(q + centre) <= size: rounding is monotonic, so each is found by halving.
-void edge_interval(float centre, float size, float* lo, float* hi)
-{
-    const int32_t most = order_of(3.402823466e38f);
-    int32_t a = -most, b = most;
-    while (a < b) {
-        const int32_t m = (int32_t)(((int64_t)a + b) >> 1);
-        volatile float u = float_of(m) + centre;
-        if (u >= 0.0f) b = m;
-        else a = m + 1;
-    }
-    *lo = float_of(a);
-    a = -most;
-    b = most;
-    while (a < b) {
-        const int32_t m = (int32_t)(((int64_t)a + b + 1) >> 1);
-        volatile float u = float_of(m) + centre;
-        if (u <= size) a = m;
-        else b = m - 1;
-    }
-    *hi = float_of(a);
-}
-
-}  // namespace
-
 static KEdges view_edges(const KCamera& c)
 {
-    KEdges e;
+    KEdges e = {0.0f, 0.0f, 0.0f, 0.0f, NAN};
+    if (!(fabsf(c.cx) < 0x1p59f && fabsf(c.cy) < 0x1p59f && c.W >= 0.0f && c.H >= 0.0f)) return e;
     edge_interval(c.cx, c.W, &e.xl, &e.xh);
     edge_interval(c.cy, c.H, &e.yl, &e.yh);
-    const float most = fmaxf(fmaxf(fabsf(e.xl), fabsf(e.xh)), fmaxf(fabsf(e.yl), fabsf(e.yh)));
-    e.margin = most < 0x1p60f ? most * 0x1p-22f : NAN;
+    e.margin = fmaxf(fmaxf(fabsf(e.xl), fabsf(e.xh)), fmaxf(fabsf(e.yl), fabsf(e.yh))) * 0x1p-22f;
     return e;
 }
 
