@@ -242,7 +242,7 @@ class Camera:
     r_min_px: float = 0.0
 
     def to_c(self) -> gs_camera:
-        return gs_camera.from_buffer_copy(self._packed())
+        return gs_camera.from_buffer_copy(self._packed()) if type(self) is Camera else self._by_field()
 
     def _packed(self) -> bytes:
         """The bytes of to_c()."""
@@ -270,10 +270,16 @@ class Camera:
         return c
 
 
+def _structs(kind, own, items):
+    """The items' structures in one array (of one, if there are none).  Items
+    of another type than our own, subclasses among them, go by their to_c()."""
+    if len(items) > 0 and all([type(x) is own for x in items]):
+        return (kind * len(items)).from_buffer_copy(b"".join([x._packed() for x in items]))
+    return (kind * max(len(items), 1))(*[x.to_c() for x in items])
+
+
 def _cameras_c(cams: Sequence[Camera]):
-    if len(cams) == 0:
-        return (gs_camera * 1)()
-    return (gs_camera * len(cams)).from_buffer_copy(b"".join([c._packed() for c in cams]))
+    return _structs(gs_camera, Camera, cams)
 
 
 def gs_visibility(means, cam: Camera, mask=None, vis_idx=None, vis_count=None, radius=None, stream=None) -> None:
@@ -327,7 +333,8 @@ class Group:
         return found.pop() if found else 0
 
     def to_c(self) -> gs_group:
-        return gs_group.from_buffer_copy(self._packed())
+        # a subclass may have another dim or stride()
+        return gs_group.from_buffer_copy(self._packed()) if type(self) is Group else self._by_field()
 
     def _packed(self) -> bytes:
         """The bytes of to_c()."""
@@ -417,9 +424,7 @@ class StepConfig:
 
 
 def _groups_c(groups: Sequence[Group]):
-    if len(groups) == 0:
-        return (gs_group * 1)()
-    return (gs_group * len(groups)).from_buffer_copy(b"".join([g._packed() for g in groups]))
+    return _structs(gs_group, Group, groups)
 
 
 def adamw_gs_step(groups: Sequence[Group], n: int, step_count, cfg: StepConfig, visible=None, vis_idx=None,
