@@ -94,6 +94,9 @@ _GROUP = struct.Struct("@4P4i3d")
 _CONFIG = struct.Struct("@4dQq4i3df7i0d3di0d2d")
 assert (_CAMERA.size, _GROUP.size, _CONFIG.size) == tuple(map(ctypes.sizeof, (gs_camera, gs_group, gs_step_config)))
 
+# what a value that a structure cannot pack raises; it then goes field by field
+_UNPACKABLE = (struct.error, TypeError, ValueError, OverflowError, AttributeError, RuntimeError)
+
 _TENSORS = (torch.Tensor, torch.nn.Parameter)     # what the short paths below take; the rest go the long way
 _device_of = getattr(torch._C, "_cuda_getDevice", None)
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
@@ -253,7 +256,7 @@ class Camera:
             if len(v) == 12:
                 return _CAMERA.pack(*v, self.fx, self.fy, self.cx, self.cy, int(self.width), int(self.height),
                                     self.z_near, self.z_far, self.r_min_px)
-        except Exception:
+        except _UNPACKABLE:
             pass
         return bytes(self._by_field())
 
@@ -349,7 +352,7 @@ class Group:
                     return _GROUP.pack(p.data_ptr(), 0 if g is None else g.data_ptr(), m.data_ptr(), v.data_ptr(),
                                        s[1] if len(s) > 1 else 1, self.dar_kind, self.reg_mode, 0, self.lr,
                                        self.dar_lambda, self.dar_clip)
-                except Exception:
+                except _UNPACKABLE:
                     pass
         return bytes(self._by_field())
 
@@ -399,7 +402,7 @@ class StepConfig:
                 int(self.unit), int(bool(self.noise_enable)), int(ng[0]), int(ng[1]), int(ng[2]), int(ng[3]), 0,
                 self.noise_lr, self.noise_k, self.noise_t, int(bool(self.aiu_enable)), self.aiu_ratio,
                 self.aiu_scale))
-        except Exception:
+        except _UNPACKABLE:
             return self._by_field()
 
     def _by_field(self) -> gs_step_config:

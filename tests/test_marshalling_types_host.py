@@ -1,7 +1,9 @@
 """Cameras and groups of other types than the binding's own, subclasses among
-them, reach the calls as their own to_c(), dim and stride() say."""
+them, reach the calls as their own to_c(), dim and stride() say; and an error
+that is not a value's passes through instead of turning into the slow way."""
 import ctypes
 
+import pytest
 import torch
 
 import paper_2601_16736_amd as gs
@@ -59,3 +61,15 @@ def test_groups_of_other_types():
     assert [g.dim for g in got] == [4, 4, 4, 4]
     assert bytes(got[2]) == bytes(own._by_field()) == bytes(got[0])
     assert flat.to_c().dim == 4
+
+
+@pytest.mark.parametrize("make,item", [(gs._cameras_c, gs.Camera(VIEW, 5.0, 5.0, 3.0, 2.0, 6, 4)),
+                                       (gs._groups_c, _group())])
+def test_other_errors_pass_through(make, item, monkeypatch):
+    class Broken:
+        def pack(self, *_):
+            raise KeyError("packing")
+
+    monkeypatch.setattr(gs, "_CAMERA" if make is gs._cameras_c else "_GROUP", Broken())
+    with pytest.raises(KeyError):
+        make([item])
