@@ -95,7 +95,7 @@ _CONFIG = struct.Struct("@4dQq4i3df7i0d3di0d2d")
 assert (_CAMERA.size, _GROUP.size, _CONFIG.size) == tuple(map(ctypes.sizeof, (gs_camera, gs_group, gs_step_config)))
 
 # what a value that a structure cannot pack raises; it then goes field by field
-_UNPACKABLE = (struct.error, TypeError, ValueError, OverflowError, AttributeError, RuntimeError)
+_UNPACKABLE = (struct.error, TypeError, ValueError, OverflowError, AttributeError, LookupError, RuntimeError)
 
 _TENSORS = (torch.Tensor, torch.nn.Parameter)     # what the short paths below take; the rest go the long way
 _device_of = getattr(torch._C, "_cuda_getDevice", None)

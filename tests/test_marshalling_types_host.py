@@ -68,8 +68,8 @@ def test_groups_of_other_types():
 def test_other_errors_pass_through(make, item, monkeypatch):
     class Broken:
         def pack(self, *_):
-            raise KeyError("packing")
+            raise NameError("packing")
 
     monkeypatch.setattr(gs, "_CAMERA" if make is gs._cameras_c else "_GROUP", Broken())
-    with pytest.raises(KeyError):
+    with pytest.raises(NameError):
         make([item])
