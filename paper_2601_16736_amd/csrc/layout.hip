@@ -282,6 +282,8 @@ __global__ __launch_bounds__(kTileThreads) void move_pairs_kernel(const void* __
     const uint2 count = reinterpret_cast<const uint2*>(counts)[(int64_t)blockIdx.x * (kDigits / 2) + threadIdx.x];
 #pragma unroll
     for (int k = 0; k < kDigits / 64; ++k) s_rank[wave][k * 64 + lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 
     uint32_t rank[kTileRounds];
 #pragma unroll
