@@ -407,16 +407,18 @@ template <typename T>
 void launch_gather(const void* src, void* dst, const int32_t* perm, int64_t n, int64_t row_bytes, hipStream_t stream)
 {
     const int64_t cpr = row_bytes / (int64_t)sizeof(T);
-    const int64_t per = kGatherThreads * kGatherUnroll<T>;
-    // places in a row and a block are exact in FP32 below 2^24
-    if (sizeof(T) == 16 || cpr > (int64_t)1 << 22 || cpr > kMaxGridBlocks * per / n) {
-        hipLaunchKernelGGL(gather_strided_kernel<T>, dim3(8192), dim3(kGatherThreads), 0, stream, (const T*)src,
-                           (T*)dst, perm, n, cpr);
-        return;
+    if constexpr (sizeof(T) < 16) {
+        // places in a row and a block are exact in FP32 below 2^24
+        const int64_t per = kGatherThreads * kGatherUnroll<T>;
+        if (cpr <= (int64_t)1 << 22 && cpr <= kMaxGridBlocks * per / n) {
+            const unsigned blocks = (unsigned)((n * cpr + per - 1) / per);
+            hipLaunchKernelGGL(gather_kernel<T>, dim3(blocks), dim3(kGatherThreads), 0, stream, (const T*)src, (T*)dst,
+                               perm, n, (uint32_t)cpr, 1.0f / (float)cpr);
+            return;
+        }
     }
-    const unsigned blocks = (unsigned)((n * cpr + per - 1) / per);
-    hipLaunchKernelGGL(gather_kernel<T>, dim3(blocks), dim3(kGatherThreads), 0, stream, (const T*)src, (T*)dst, perm,
-                       n, (uint32_t)cpr, 1.0f / (float)cpr);
+    hipLaunchKernelGGL(gather_strided_kernel<T>, dim3(8192), dim3(kGatherThreads), 0, stream, (const T*)src, (T*)dst,
+                       perm, n, cpr);
 }
 
 // Below this many primitives ten launches take longer than the library's sort,
