@@ -29,7 +29,8 @@ __device__ __forceinline__ bool visible_any(float x, float y, float z, const flo
     return v;
 }
 
-template <bool BF16, int UNIT, bool NOISE, bool RADIUS, bool PACKED, typename CAMS>
+// THREES: some group may go three elements at a time (KGroup::vec).
+template <bool BF16, int UNIT, bool NOISE, bool RADIUS, bool PACKED, typename CAMS, bool THREES = true>
 __global__ __launch_bounds__(kBlock) void step_view_kernel(KScene S, KHyper H, CAMS cam,
                                                            const float* __restrict__ means, int64_t ms,
                                                            const float* __restrict__ radius,
@@ -78,9 +79,8 @@ __global__ __launch_bounds__(kBlock) void step_view_kernel(KScene S, KHyper H, C
         stage_step_rows(nrows, s_row[wave], s_rb1[wave], s_rsb2[wave], S.t, H,
                         d_stream(seed, kTagRsr, H.iteration), lane);
         wave_sync();
-        step_all_groups<BF16, NOISE, BF16 ? GS_STEP_UNROLL_BF16 : GS_STEP_UNROLL, PACKED>(S, H, seed, nrows, s_row[wave],
-                                                                                  s_rb1[wave], s_rsb2[wave], lane,
-                                                                                  s_noise[wave]);
+        step_all_groups<BF16, NOISE, BF16 ? GS_STEP_UNROLL_BF16 : GS_STEP_UNROLL, PACKED, THREES>(
+            S, H, seed, nrows, s_row[wave], s_rb1[wave], s_rsb2[wave], lane, s_noise[wave]);
     }
     if (H.rsr_thr == 0 && H.aiu_thr == 0) return;
 
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kBlock) void step_view_kernel(KScene S, KHyper H, C
     }
     if (nrows == 0) return;
     wave_sync();
-    invisible_all_groups<BF16>(S, H, seed, nrows, s_row[wave], s_rb1[wave], s_rsb2[wave], lane);
+    invisible_all_groups<BF16, THREES>(S, H, seed, nrows, s_row[wave], s_rb1[wave], s_rsb2[wave], lane);
 }
 
 namespace {
@@ -148,13 +148,48 @@ ViewFn<CAMS> pick_view(bool bf16, int unit, bool noise, bool radius)
     return radius ? pick_view<false, false, true, PACKED, CAMS>(unit) : pick_view<false, false, false, PACKED, CAMS>(unit);
 }
 
+// The plain FP32 step of a scene whose rows of threes are single accesses: the
+// kernel without those passes, such rows one by one (us, without / with them:
+// 160,000 rows 41.8 / 42.0, 250,000 unsorted 42.7 / 43.2, 300,000 unsorted with
+// Re-State and AIU 66.0 / 67.0; from a million rows on the same).  BF16 scenes
+// take one kernel (within 0.2 % of one without them).
+template <bool RADIUS, typename CAMS>
+ViewFn<CAMS> pick_view_without_threes(int unit)
+{
+    switch (unit) {
+    case 32: return step_view_kernel<false, 32, false, RADIUS, false, CAMS, false>;
+    case 64: return step_view_kernel<false, 64, false, RADIUS, false, CAMS, false>;
+    case 128: return step_view_kernel<false, 128, false, RADIUS, false, CAMS, false>;
+    case 256: return step_view_kernel<false, 256, false, RADIUS, false, CAMS, false>;
+    default: return nullptr;
+    }
+}
+
+// Makes the rows of three elements go one by one, if there are no wider ones of threes.
+bool without_threes(KScene& s)
+{
+    for (int g = 0; g < s.n_groups; ++g)
+        if (s.g[g].vec == 3 && s.g[g].cpr > 1) return false;
+    for (int g = 0; g < s.n_groups; ++g)
+        if (s.g[g].vec == 3) {
+            s.g[g].vec = 1;
+            s.g[g].cpr = s.g[g].dim;
+        }
+    return true;
+}
+
 template <typename CAMS>
-hipError_t launch_view(const KScene& s, const KHyper& h, const CAMS& cams, const float* means, int64_t ms,
+hipError_t launch_view(KScene s, const KHyper& h, const CAMS& cams, const float* means, int64_t ms,
                        const float* radius, uint8_t* mask_out, hipStream_t stream)
 {
     if (s.n == 0) return hipSuccess;
-    ViewFn<CAMS> fn = s.pk_stride > 0 ? pick_view<true, CAMS>(s.bf16 != 0, s.unit, h.noise != 0, radius != nullptr)
-                                      : pick_view<false, CAMS>(s.bf16 != 0, s.unit, h.noise != 0, radius != nullptr);
+    ViewFn<CAMS> fn;
+    if (s.pk_stride == 0 && s.bf16 == 0 && h.noise == 0 && without_threes(s))
+        fn = radius != nullptr ? pick_view_without_threes<true, CAMS>(s.unit)
+                               : pick_view_without_threes<false, CAMS>(s.unit);
+    else
+        fn = s.pk_stride > 0 ? pick_view<true, CAMS>(s.bf16 != 0, s.unit, h.noise != 0, radius != nullptr)
+                             : pick_view<false, CAMS>(s.bf16 != 0, s.unit, h.noise != 0, radius != nullptr);
     if (fn == nullptr) return hipErrorInvalidValue;
     const int64_t units = (s.n + s.unit - 1) / s.unit;
     const unsigned blocks = (unsigned)((units + kWavesPerBlock - 1) / kWavesPerBlock);
