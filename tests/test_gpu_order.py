@@ -1,4 +1,4 @@
-"""gs_spatial_order at the edges of its tiles (4096 primitives, 1024 to a wave)
+"""gs_spatial_order at the edges of its tiles (4096 primitives, 512 to a wave)
 and digits: the stable order of the host's Morton codes, exactly; eagerly and
 from a captured graph replayed on other means."""
 import numpy as np
